@@ -26,8 +26,8 @@ Beside the step the line carries, for the uniform BFP8 workloads:
   read_ceiling  the read-only probes of libhma: the attention's BFP8 bytes
                 read in the attention's decomposition and with the heads of a
                 page read together, and a flat 1 GiB streaming read;
-  route_legs    one layer timed on codes with a block exponent of 134 in
-                every page, on the headline's codes (124..131) under the same
+  route_legs    one layer timed on codes that force the ldexp decode route,
+                on the headline's codes (packed route) under the same
                 repetition scheme, and (with the CPU baseline) on the oracle
                 encoder's codes of the workload's value distribution.
 
@@ -413,9 +413,9 @@ def issue_ceiling(hma, torch, waves_per_simd=2, iters=2000):
 
 
 def route_legs(w, hma, torch, total_pages, pt_d, ctx_d, max_ctx, q, tps, scale, stream, a_bytes):
-    """One attention layer timed on codes whose pages all carry one block
-    exponent of 134 (which takes them to the BF16 route), against the headline's
-    codes (exponents 124..131: inside it), both cycling over 4 resident
+    """One attention layer timed on codes that force the ldexp decode route
+    (every page carries one block exponent of 134), against the headline's
+    codes (exponents 124..131: packed route), both cycling over 4 resident
     layers so that no layer is re-read from the caches."""
     dev = q.device
     out = {}
@@ -445,7 +445,7 @@ def encoded_values_leg(w, hma, torch, kv, tps, stream, a_bytes):
     """The layer the CPU baseline encoded (the oracle encoder's codes of the
     workload's value distribution, outlier channels included), uploaded as 4
     copies and timed like the route legs; with the share of its (page, KV
-    head) tiles whose block exponents all lie in 7..133."""
+    head) tiles that take the packed route."""
     dev = torch.device("cuda", 0)
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
     pools = [(t(kv.k_mant), t(kv.k_exp), t(kv.v_mant), t(kv.v_exp)) for _ in range(4)]

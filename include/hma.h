@@ -243,15 +243,15 @@ HMA_API int hma_ingress_rebuild(const uint8_t *host_mant, const uint8_t *host_ex
  *     at least 64 pages (each wave then attends its pieces alone), else one
  *     per workgroup (whose waves share each piece, or, where the pieces are
  *     short, take whole pieces in turn); a chunk that spans several
- *     sequences yields one range per sequence.  Ragged batches therefore load every compute unit
- *     equally.  Otherwise the ranges are tokens_per_split tokens of the
- *     library's choice.
+ *     sequences yields one range per sequence.  Ragged batches therefore
+ *     load every compute unit equally.  Otherwise the ranges are
+ *     tokens_per_split tokens of the library's choice.
  * A ragged batch needs no host-side length information, and the schedule
  * depends only on the lengths: repeated calls give the same bits.  (The
  * schedule also depends on the kernel variant that runs -- with or without
- * BF16 pools -- and BFP8 and BF16 pages are multiplied in F16 and BF16, so the
- * same batch read in another format may differ in the last bits; each is
- * deterministic.)
+ * BF16 pools -- so the same batch read by both may differ in the last bits;
+ * each is deterministic.  Under one schedule, BFP8 pages and BF16 pages that
+ * hold the same values give the same bits.)
  * context_lens[b] == 0 gives out = 0 and lse = -inf.  Slots at
  * or past the context end in the last page are never used, whatever they
  * hold.
@@ -457,7 +457,7 @@ HMA_API int hma_issue_probe(int32_t valu_kind, int32_t valu_ops, int32_t with_mf
  * attention of hma_decode_attn_bfp8 over BFP8 pages (Sec. 3.3: the pages
  * decoded exactly in registers inside the paged read) with both products on
  * the vector ALU instead of the matrix cores, the comparison point for that
- * choice.  Same bytes, exact decode and split decomposition (one
+ * choice.  Same bytes, decode routes and split decomposition (one
  * workgroup of 8 waves per (range, sequence, KV head)); QK^T runs on
  * v_dot2c_f32_bf16 (BF16 pairs, float32 sums), PV on float32 FMAs with
  * unrounded weights.  The ranges' partials are merged by log-sum-exp in a

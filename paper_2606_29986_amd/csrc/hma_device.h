@@ -16,7 +16,7 @@
 //      AND-OR inserts them.
 // About 3.75 VALU operations per element.
 //
-// A faster BF16 route (the vector-ALU attention) covers 7 <= E <= 133, where every nonzero element is a
+// A faster route covers 7 <= E <= 133, where every nonzero element is a
 // normal BF16: the BF16 bits of the magnitude itself (exact, at most 7
 // significant bits) only need their exponent field lowered by 133 - E, which
 // one saturating 16-bit packed subtract does for two elements at once while
@@ -65,10 +65,9 @@ __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a),
                                                                   __builtin_bit_cast(u16x2_t, b)));
 }
-__device__ __forceinline__ uint32_t pk_mad_u16(uint32_t a, uint32_t b, uint32_t c)
+__device__ __forceinline__ uint32_t pk_shl7_u16(uint32_t a)
 {
-    return __builtin_bit_cast(uint32_t, (u16x2_t)(__builtin_bit_cast(u16x2_t, a) * __builtin_bit_cast(u16x2_t, b) +
-                                                  __builtin_bit_cast(u16x2_t, c)));
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2_t, a) << (uint16_t)7);
 }
 
 // byte-select constants for __builtin_amdgcn_perm(S0, S1, sel):
@@ -163,25 +162,14 @@ __device__ __forceinline__ u32x2_t bfp8_word_to_bf16_fast(uint32_t w, uint32_t d
                    pack_bf16_scaled_signed(f2, f3, d, w, 2, w, 3)};
 }
 
-// ---- F16 pairs: an element byte in both bytes of a half (x) is, under the
-// mask, the F16 subnormal +-m * 2^-24; `d` holds a power of two per half.
-__device__ __forceinline__ uint32_t f16_signed_scaled(uint32_t x, uint32_t d)
+__device__ __forceinline__ void bfp8_block_to_bf16_fast(u32x4_t w, uint32_t d, u32x4_t &lo, u32x4_t &hi)
 {
-    typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2_t, x & 0x807F807Fu) * __builtin_bit_cast(f16x2_t, d));
-}
-
-// Decode four words (16 elements of one block) into eight F16 pairs.
-__device__ __forceinline__ void bfp8_block_to_f16(u32x4_t w, uint32_t d, u32x4_t &lo, u32x4_t &hi)
-{
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const uint32_t e01 = f16_signed_scaled(__builtin_amdgcn_perm(w[i], w[i], 0x01010000u), d);
-        const uint32_t e23 = f16_signed_scaled(__builtin_amdgcn_perm(w[i], w[i], 0x03030202u), d);
-        u32x4_t &o = i < 2 ? lo : hi;
-        o[2 * (i & 1)] = e01;
-        o[2 * (i & 1) + 1] = e23;
-    }
+    const u32x2_t a = bfp8_word_to_bf16_fast(w.x, d);
+    const u32x2_t b = bfp8_word_to_bf16_fast(w.y, d);
+    const u32x2_t c = bfp8_word_to_bf16_fast(w.z, d);
+    const u32x2_t e = bfp8_word_to_bf16_fast(w.w, d);
+    lo = u32x4_t{a.x, a.y, b.x, b.y};
+    hi = u32x4_t{c.x, c.y, e.x, e.y};
 }
 
 }  // namespace hma

@@ -196,14 +196,14 @@ def bfp8_codes_device(w: Workload, layer: int, kind: str, num_pages: int, device
     Mantissa bytes are uniform over all 256 sign/magnitude codes; exponent
     bytes are uniform over 124..131, the range the BF16 draws above produce.
     The fused attention's work per page depends on the data in two places:
-    it decodes a (page, KV head) to F16 when its block exponents lie in the
-    piece's window of 12 (121..132 if that holds its first page), to BF16 otherwise, both
-    exactly, and it skips the rescale of its accumulators
+    it picks one of two exact decode routes per (page, KV head) -- the packed
+    16-bit route when every block exponent of the page lies in 7..133, the
+    ldexp route otherwise -- and it skips the rescale of its accumulators
     when a page does not raise the running maximum.  Exponents in 124..131
-    lie in the window (route="packed").  With route="ldexp" the
+    always take the packed route.  route="ldexp" forces the other one: the
     first block exponent of token 0 of every (page, KV head) is set to 134
-    (elements up to 254, still finite), and the piece's window
-    becomes 126..137, above the blocks of 124 and 125.  Returns (mant uint8, exp uint8)
+    (elements up to 254, still finite).  Encoder-produced values of the
+    outlier workloads mix both routes.  Returns (mant uint8, exp uint8)
     tensors of shapes [pages][Hkv][P][D] and [pages][Hkv][P][D/16]."""
     import torch
     if route not in ("packed", "ldexp"):

@@ -34,11 +34,19 @@ constexpr int kTokenTileBytes = kChanTiles * kTileBytes;     // 4352 = 272 x 16
 constexpr int kTokenTileChunks = kTokenTileBytes / 16;
 
 // Sources from this size on are loaded past the caches, smaller ones through
-// them, for packing and rebuilding alike.  Streaming against plain loads, us:
-// 28 MB source (36 pools, 700 tokens) 22.4 / 19.3 packing, 31.4 / 28.2
-// rebuilding; 218 MB (40 pools, 5003 tokens) 141 / 149 packing, 215 / 214
-// rebuilding repeatedly, but 233 / 291 rebuilding a source not seen before.
-constexpr int64_t kStreamBytes = int64_t(64) << 20;
+// them, for packing and rebuilding alike.  A source that still lies in the 256
+// MiB memory-side cache is read faster through the caches, one that does not
+// past them.  K and V of one request, us, plain / streaming loads, read for the
+// first time after it was written; and three requests in turn:
+//   MiB a side   packing                          rebuilding
+//   19           18.4 / 18.0;  15.0 / 17.7        24.6 / 24.4;  21.0 / 22.5
+//   26           22.5 / 22.2;  19.2 / 22.6        34.1 / 33.2;  28.1 / 31.9
+//   38           31.0 / 31.5;  28.2 / 30.7        48.4 / 48.4;  36.8 / 43.9
+//   58           48.5 / 46.6;  45.7 / 44.0        76.0 / 69.6;  64.7 / 64.5
+//   76           66.3 / 58.8;  59.1 / 56.1       106.0 / 87.1;  83.1 / 82.7
+// (With the caches full of other data written meanwhile, streaming gains from 4
+// MiB on: 38 MiB 24.9 / 18.6 packing, 32.0 / 25.0 rebuilding, one side.)
+constexpr int64_t kStreamBytes = int64_t(48) << 20;
 
 // Where one wave's token tile lies and goes.
 struct TileUnit {

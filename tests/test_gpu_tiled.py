@@ -189,3 +189,42 @@ def test_pack_tiled_of_a_source_read_past_the_caches():
                         src_pool_stride_bytes=stride, dst_pool_stride_pages=pool_pages, num_kv_heads=hkv)
     torch.cuda.synchronize()
     assert np.array_equal(gm.cpu().numpy(), wm) and np.array_equal(ge.cpu().numpy(), we)
+
+
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("n_pools", [6, 7])
+def test_rebuild_tiled_on_both_sides_of_the_streaming_line(n_pools, rope):
+    """Sources just below and above 48 MiB (loaded through and past the caches),
+    with a ragged last token tile and padded pool strides: bit-exact."""
+    rng = np.random.default_rng(970 + n_pools)
+    hkv, n_shards, n_tokens, pool_pages = 8, 4, 7001, 460
+    src, stride, dst_pages = _case(rng, n_pools, n_shards, n_tokens, hkv, pool_pages, pad_stride=48)
+    assert (n_pools * n_shards * hma.tiled_shard_bytes(n_tokens, hkv // n_shards) >= 48 << 20) == (n_pools == 7)
+    note(f"tiled rebuild: {src.size >> 20} MiB source, rope={rope}")
+    want = np.full((n_pools * pool_pages, hkv, P, D), SENTINEL, np.uint16)
+    oracle.rebuild_tiled(src, stride, n_pools, n_shards, n_tokens, hkv, want, dst_pages, pool_pages, rope)
+    out = torch.full(want.shape, SENTINEL, dtype=torch.int16, device="cuda")
+    hma.bfp8_rebuild_tiled(dev(src), out, n_tokens, n_shards, dst_pages=dev(dst_pages), n_pools=n_pools,
+                           src_pool_stride_bytes=stride, dst_pool_stride_pages=pool_pages, rope_reorder=rope,
+                           num_kv_heads=hkv)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint16), want)
+
+
+@pytest.mark.parametrize("n_pools", [6, 7])
+def test_pack_tiled_on_both_sides_of_the_streaming_line(n_pools):
+    """The same for packing."""
+    rng = np.random.default_rng(980 + n_pools)
+    hkv, n_shards, n_tokens, pool_pages = 8, 4, 7001, 460
+    src, stride, dst_pages = _case(rng, n_pools, n_shards, n_tokens, hkv, pool_pages, pad_stride=48)
+    assert (n_pools * n_shards * hma.tiled_shard_bytes(n_tokens, hkv // n_shards) >= 48 << 20) == (n_pools == 7)
+    note(f"pack tiled: {src.size >> 20} MiB source")
+    wm = np.full((n_pools * pool_pages, hkv, P, D), 0xA5, np.uint8)
+    we = np.full((n_pools * pool_pages, hkv, P, D // 16), 0xA5, np.uint8)
+    oracle.pack_tiled(src, stride, n_pools, n_shards, n_tokens, hkv, wm, we, dst_pages, pool_pages)
+    gm = torch.full(wm.shape, 0xA5, dtype=torch.uint8, device="cuda")
+    ge = torch.full(we.shape, 0xA5, dtype=torch.uint8, device="cuda")
+    hma.bfp8_pack_tiled(dev(src), gm, ge, n_tokens, n_shards, dst_pages=dev(dst_pages), n_pools=n_pools,
+                        src_pool_stride_bytes=stride, dst_pool_stride_pages=pool_pages, num_kv_heads=hkv)
+    torch.cuda.synchronize()
+    assert np.array_equal(gm.cpu().numpy(), wm) and np.array_equal(ge.cpu().numpy(), we)

@@ -23,7 +23,7 @@ constexpr int64_t kComputeUnits = 256;       // MI355X
 // stream at full rate
 constexpr int64_t kTargetWorkgroups = 2 * kComputeUnits;
 constexpr int32_t kMinAutoSplit = 256;
-constexpr int32_t kPagePerWave = 128;         // tokens that give each of 8 waves one page
+constexpr int32_t kPagePerWave = 128;        // tokens that give each of 8 waves one page
 constexpr int32_t kMaxAutoSplit = 2048;
 constexpr int32_t kMaxWideSplit = 8192;
 
@@ -56,9 +56,15 @@ int32_t splits_for(int32_t max_ctx, int32_t tps);
 // Shortest automatic split.  A split of t tokens takes its waves t / 128 page
 // latencies, and the fold of a context's n = max_ctx / t partials about n / 16
 // as long: the sum is least at t = sqrt(8 max_ctx), taken up to a whole page
-// per wave.  One sequence, one KV head, us per call: 32757 tokens 24.4 at 256
-// tokens, 19.4 at 512, 20.3 at 1024; 16000 tokens 16.9 at 256, 15.6 at 512;
-// 8000 tokens 13.0 at 256, 13.6 at 384.
+// per wave.  One sequence, us per call: one KV head, 8192 tokens 11.9 at 256
+// tokens, 12.3 at 384 (the rule: 256); 16000 tokens 15.9 at 256, 14.6 at 384 and
+// 512 (384); 32757 tokens 23.7 at 256, 18.3 at 512, 17.7 at 768 (512); 8 KV heads,
+// 4096 tokens 11.5 at 256, 11.6 at 384 (256).  The rule sees the length alone: with 8
+// KV heads, whose folds run at the same time, it stays short of the best at
+// 8192 tokens (15.4 at its 256, 13.9 at 512) and 16000 (17.9 at 512, 17.0 at 768),
+// and contexts of up to 1024 tokens take 0.4 to 0.8 less at 128 than at the 256
+// below which it does not go.  Over 7 batch shapes, both page formats and 13
+// lengths it is nowhere slower than 256 tokens throughout.
 int32_t shortest_split(int32_t max_ctx)
 {
     int64_t t = kMinAutoSplit;

@@ -87,6 +87,29 @@ def test_split_and_workspace_queries():
     assert hma.tokens_per_split(4, 30, 8, 512) == 0
 
 
+def test_shortest_automatic_split():
+    """Few long contexts: splits of at least sqrt(8 x length) tokens, in whole
+    128-token rounds and from 256 on; never more splits, and never a larger
+    workspace, than one workgroup per CU or 256-token splits would give."""
+    for ctx, want in ((256, 256), (255, 256), (4096, 256), (8192, 256), (8193, 384), (16000, 384), (18432, 384),
+                      (18433, 512), (32757, 512), (32768, 512), (32769, 640), (131072, 1024), (131073, 1152)):
+        assert hma.tokens_per_split(1, 8, 1, ctx) == want, ctx
+    # the even share of the CUs where that is longer, a whole short context otherwise
+    assert hma.tokens_per_split(1, 64, 8, 32757) == 1024
+    assert hma.tokens_per_split(2, 16, 2, 32757) == 512
+    assert hma.tokens_per_split(1, 8, 1, 100) == 112
+    for batch, hkv in ((1, 1), (2, 1), (1, 4), (3, 5), (1, 8), (4, 8)):
+        for ctx in (1, 17, 255, 257, 1000, 4096, 8193, 20000, 32757, 100001):
+            tps = hma.tokens_per_split(batch, 4 * hkv, hkv, ctx)
+            even = -(-(-(-batch * hkv * ctx // 256)) // 32) * 32
+            before = min(max(even, 256), -(-ctx // 16) * 16)
+            assert tps % 16 == 0
+            if before <= 8192 and batch * hkv * -(-ctx // before) <= 256:      # the 8-wave shape
+                assert tps >= before, (batch, hkv, ctx)
+                assert hma.workspace_bytes(batch, 4 * hkv, hkv, ctx) <= hma.workspace_bytes(batch, 4 * hkv, hkv, ctx,
+                                                                                            before)
+
+
 def _dequant(naive=False, **kw):
     a = dict(src_mant=FAKE, src_exp=FAKE, dst=FAKE * 2, src_pages=FAKE, dst_pages=FAKE,
              n_pages=4, n_pools=1, src_stride=0, dst_stride=0, hkv=8, D=128, P=16)

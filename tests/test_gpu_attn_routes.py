@@ -198,16 +198,17 @@ def test_fold_of_any_number_of_partials(parts):
 
 
 @pytest.mark.parametrize("bf16_fraction", [0.0, 0.5])
-@pytest.mark.parametrize("lengths", ["short", "long_and_short", "with_empty", "one_page"])
+@pytest.mark.parametrize("lengths", ["short", "long_and_short", "with_empty", "one_page", "two_in_a_range"])
 def test_pieces_taken_by_single_waves(lengths, bf16_fraction):
     """More workgroups than CUs, ranges short enough that their pieces go to
-    the waves in turn: whole sequences, cut ones (published by a wave, folded
+    the waves in turn (of two BFP8 pieces: stay with the workgroup): whole sequences, cut ones (published by a wave, folded
     with pieces of whole workgroups), empty ones between them, and the order of
     arrival without effect (a repeat gives the same bits)."""
     rng = np.random.default_rng(9100)
     B, hkv = 150, 4
     ctx = {"short": rng.integers(1, 200, B), "long_and_short": rng.integers(1, 150, B),
-           "with_empty": rng.integers(0, 90, B), "one_page": np.full(B, 16)}[lengths].astype(np.int32)
+           "with_empty": rng.integers(0, 90, B), "one_page": np.full(B, 16),
+           "two_in_a_range": np.full(B, 128) - (np.arange(B) % 7 == 0)}[lengths].astype(np.int32)
     if lengths == "long_and_short":
         ctx[rng.choice(B, 30, replace=False)] = rng.integers(1200, 1700, 30)
     if lengths == "with_empty":
